@@ -554,18 +554,17 @@ hipError_t launch_gemm(const GemmArgs &g, bool f16, int epi, int kind, hipStream
   if (epi < kEpiQKV || epi > kEpiSwiGLU ||
       (epi == kEpiResidual ? (!g.h || (g.x_out && !g.ss_out)) : (!g.ss_in || g.n_ss < 4 || g.n_ss % 4 != 0)))
     return hipErrorInvalidValue;
+  if (g.a_packed != g.act_packed) return hipErrorInvalidValue;   // every kernel takes both operands in one layout
   if (g.wide > 0) return g.a_packed ? launch_gemm_rows(g, f16, epi, kind, stream) : launch_gemm_tile(g, f16, epi, kind, stream);
   const int nwg = g.n_slices * g.n_ttiles;
   const dim3 grid((nwg + 7) / 8 * 8);
   if (g.a_packed) {
-    if (!g.act_packed) return hipErrorInvalidValue;
     if (epi == kEpiSwiGLU) launch_packed<true, kEpiSwiGLU>(g, kind, grid, stream);
     else if (epi == kEpiQKV) launch_packed<false, kEpiQKV>(g, kind, grid, stream);
     else if (f16) launch_packed<true, kEpiResidual>(g, kind, grid, stream);
     else launch_packed<false, kEpiResidual>(g, kind, grid, stream);
     return hipGetLastError();
   }
-  if (g.act_packed) return hipErrorInvalidValue;   // the LDS-ring kernel reads row-major activations
   if (epi == kEpiSwiGLU) launch_epi<true, kEpiSwiGLU>(g, kind, grid, stream);
   else if (epi == kEpiQKV) launch_epi<false, kEpiQKV>(g, kind, grid, stream);
   else if (f16) launch_epi<true, kEpiResidual>(g, kind, grid, stream);
