@@ -1,6 +1,7 @@
 """Work lists of plans that take more than one round of workgroups: each item
-is on exactly one list (tests/native/plan_lists.cpp, planner sources under the
-address and undefined-behaviour sanitizers, host code only)."""
+is on exactly one list (tests/native/plan_lists.cpp), and no plan outgrows the
+library's own scratch for its lists (plan_scratch.cpp); planner sources under the
+address and undefined-behaviour sanitizers, host code only."""
 
 import os
 import shutil
@@ -14,15 +15,32 @@ CSRC = os.path.join(ROOT, "paper_2607_18839_amd", "csrc")
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
 
 
-def test_every_item_is_on_one_list(tmp_path):
-    exe = str(tmp_path / "plan_lists")
-    r = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
-                        "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
-                        os.path.join(ROOT, "tests", "native", "plan_lists.cpp"), os.path.join(CSRC, "plan.cpp"),
+def _build(tmp_path, name, flags):
+    exe = str(tmp_path / name)
+    r = subprocess.run(["g++", "-std=c++17", *flags, "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
+                        os.path.join(ROOT, "tests", "native", name + ".cpp"), os.path.join(CSRC, "plan.cpp"),
                         "-o", exe], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-3000:]
+    return exe
+
+
+SANITIZE = ["-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all"]
+
+
+def test_every_item_is_on_one_list(tmp_path):
+    exe = _build(tmp_path, "plan_lists", SANITIZE)
     for seed in range(3):
         r = subprocess.run([exe, str(seed)], capture_output=True, text=True, timeout=300)
         assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
         lists, forks, paged, single = map(int, r.stdout.split())
         assert lists > 50 and forks and paged and single, r.stdout
+
+
+def test_lists_keep_the_scratch_limit(tmp_path):
+    """A plan that hpd_branch_attn_step_noalloc accepts without lists is accepted with them."""
+    exe = _build(tmp_path, "plan_scratch", SANITIZE)
+    for seed in range(3):
+        r = subprocess.run([exe, str(seed)], capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
+        fitted, lists, _ = map(int, r.stdout.split())
+        assert fitted > 100 and lists > 100, r.stdout
