@@ -1,7 +1,9 @@
 """Work lists of plans that take more than one round of workgroups: each item
 is on exactly one list (tests/native/plan_lists.cpp), and no plan outgrows the
-library's own scratch for its lists (plan_scratch.cpp); planner sources under the
-address and undefined-behaviour sanitizers, host code only."""
+library's own scratch for its lists (plan_scratch.cpp), private items are spread
+over the workgroups (plan_spread.cpp), and the lists do not slow the planner
+(plan_time.cpp).  Planner sources under the address and undefined-behaviour
+sanitizers, host code only."""
 
 import os
 import shutil
@@ -44,6 +46,14 @@ def test_lists_keep_the_scratch_limit(tmp_path):
         assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
         fitted, lists, _ = map(int, r.stdout.split())
         assert fitted > 100 and lists > 100, r.stdout
+
+
+def test_private_items_are_spread(tmp_path):
+    exe = _build(tmp_path, "plan_spread", SANITIZE)
+    for seed in range(3):
+        r = subprocess.run([exe, str(seed)], capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
+        assert int(r.stdout) > 50, r.stdout
 
 
 def test_lists_do_not_slow_the_planner(tmp_path):
