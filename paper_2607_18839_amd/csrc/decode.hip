@@ -59,10 +59,10 @@ DecodeLayout decode_layout(const hpd_model_desc &m, const Plan &P) {
   L.nq = P.attn.num_q_heads * HPD_HEAD_DIM;
   L.nkv = P.attn.num_kv_heads * HPD_HEAD_DIM;
   const bool packed = m.weight_format == HPD_WEIGHTS_PACKED;
-  L.s_qkv = choose_gemm(L.nq + 2 * L.nkv, L.H, L.Tpad, packed, false);
-  L.s_o = choose_gemm(L.H, L.nq, L.Tpad, packed, false);
-  L.s_gu = choose_gemm(2 * L.I, L.H, L.Tpad, packed, true);
-  L.s_down = choose_gemm(L.H, L.I, L.Tpad, packed, true);
+  L.s_qkv = choose_gemm(L.nq + 2 * L.nkv, L.H, L.Tpad, packed, false, kEpiQKV);
+  L.s_o = choose_gemm(L.H, L.nq, L.Tpad, packed, false, kEpiResidual);
+  L.s_gu = choose_gemm(2 * L.I, L.H, L.Tpad, packed, true, kEpiSwiGLU);
+  L.s_down = choose_gemm(L.H, L.I, L.Tpad, packed, true, kEpiResidual);
   size_t off = align256(P.workspace_bytes);
   auto take = [&](size_t bytes) {
     const size_t at = off;

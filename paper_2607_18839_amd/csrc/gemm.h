@@ -109,11 +109,11 @@ hipError_t launch_lm_argmax(const GemmArgs &g, int kind, hipStream_t stream);
 // Workgroup shape of a projection: rg row groups in the skinny kernels (wide =
 // 0), or token tiles per workgroup of the many-token kernels: 1, 2 or 4
 // (packed operands, launch_gemm_rows: 128 weight rows per workgroup), 2 or 4
-// (row-major operands, launch_gemm_tile: 64 or 128 weight rows).  f16: the
-// MLP's projections.
+// (row-major operands, launch_gemm_tile: 64 or 128 weight rows).  f16 and epi
+// as for launch_gemm.
 struct GemmShape {
   int rg, wide;
 };
-GemmShape choose_gemm(int N, int K, int Tpad, bool packed, bool f16);
+GemmShape choose_gemm(int N, int K, int Tpad, bool packed, bool f16, int epi);
 
 }  // namespace hpd

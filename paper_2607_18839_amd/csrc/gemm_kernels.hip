@@ -596,49 +596,61 @@ int choose_rg(int N, int K, int tiles) {
 
 }  // namespace
 
-// The kernel and its workgroup shape for an N x K projection over Tpad
-// tokens, by an estimate in us of each: a fixed part (launch, first loads,
-// epilogue), then per round of 256 workgroups (one per CU) the measured time
-// of a K step, or for the skinny kernels that of the bytes a CU loads (every
-// wave its own 64 rows).  Measured per launch on one box, hidden 1024,
-// intermediate 3072, 16 heads (skinny kernel / the shape taken):
-//   packed, QKV, O, gate/up, down at 1,256 tokens: 13.7 / 7.8, 13.6 / 9.1,
-//     51.1 / 21.8, 29.5 / 16.8 us; at 272 tokens: 6.4 / 6.0, 6.8 / 6.0,
-//     14.3 / 7.9 us, down skinny (10.8 against 11.2); at 129 tokens: gate/up
-//     8.5 / 6.5, the others skinny (4.3, 4.4, 6.1 against 6.0, 5.9, 10.6)
-//   torch layout at 1,256 tokens: 12.9 / 9.9, 12.9 / 11.5, 58.4 / 28.2,
-//     38.3 / 23.2; at 129 and 33 tokens gate/up 11.9 / 10.1
-//     and 10.4 / 8.0, the others skinny
-// (hidden 2048, intermediate 6144, 564 tokens, packed: 23.2 / 14.0,
-// 13.0 / 10.0, 85.1 / 38.1, 55.2 / 35.5.)
-GemmShape choose_gemm(int N, int K, int Tpad, bool packed, bool f16) {
-  const int tiles = Tpad / kGemmTile, steps = K / kGemmKStep;
+// The kernel and its workgroup shape for an N x K projection over Tpad tokens:
+// the one with the least estimated time.  Fitted to the times of every shape for
+// the four projections inside decode steps whose weights come from memory (eight
+// models of hidden 256 to 4096, 1 to 48 token tiles; checked on three more).
+// Launched alone with warm weights a kernel shows other crossovers: by those, down
+// at hidden 2048 and 5 to 8 tiles took 128 rows x 1 tile, 10 to 12 us slower than
+// the skinny kernel, and 128 rows x 4 tiles were never taken, though gate/up at
+// hidden 2048 and 32 to 48 tiles is 10 to 14 us faster so.  Over those 2,288
+// projections the choice costs 0.04 % of a layer's time on average against the
+// best shape of each, 0.70 % by the former rule.
+GemmShape choose_gemm(int N, int K, int Tpad, bool packed, bool f16, int epi) {
+  // us: a fixed part (launch, first loads, epilogue), a K step of a launch of up
+  // to one workgroup per CU and of each round of 256 of a larger one, and the
+  // part of the last round that is shared out among the CUs.
+  struct Times {
+    double fixed, first, round, shared;
+  };
+  // [packed][bf16; fp16 gate/up; fp16 down]
+  static constexpr Times kSkinny[2][3] = {
+      {{3.5, 0.18, 0.313, 0.4}, {3.9, 0.38, 0.43, 0.07}, {3.6, 0.325, 0.4, 0.03}},
+      {{3.35, 0.18, 0.323, 0.07}, {3.4, 0.2, 0.377, 0.2}, {3.55, 0.2, 0.347, 0.17}}};
+  // [bf16; fp16 gate/up; fp16 down]: 1, 2 and 4 token tiles by 128 rows (packed)
+  static constexpr Times kRows[3][3] = {
+      {{3.05, 0.166, 0.206, 0.42}, {3.35, 0.25, 0.264, 0.7}, {4.9, 0.36, 0.54, 1.0}},
+      {{3.1, 0.19, 0.213, 0.3}, {3.15, 0.278, 0.255, 0.41}, {3.65, 0.39, 0.405, 0.0}},
+      {{2.8, 0.184, 0.198, 0.33}, {3.1, 0.275, 0.243, 0.42}, {3.9, 0.405, 0.381, 0.0}}};
+  // 2 token tiles by 64 rows and 4 by 128 (row-major)
+  static constexpr Times kTile[3][2] = {{{3.55, 0.118, 0.22, 0.57}, {4.05, 0.74, 0.605, 0.66}},
+                                        {{3.95, 0.187, 0.25, 0.57}, {3.25, 0.784, 0.715, 0.44}},
+                                        {{3.4, 0.203, 0.261, 0.3}, {3.65, 0.83, 0.7, 0.27}}};
+  const int tiles = Tpad / kGemmTile, steps = K / kGemmKStep, use = !f16 ? 0 : epi == kEpiSwiGLU ? 1 : 2;
   GemmShape best{choose_rg(N, K, tiles), 0};
-  auto rounds = [](double wgs) { return std::max(1.0, std::ceil(wgs / 256.0)); };
-  double cost = 1e30;
-  if (best.rg > 0) {
-    const double kb = 4 * 64 * (K / (4 / best.rg)) * 2 / 1024.0;
-    cost = 3.4 + (packed ? 0.0125 : 0.0165) * kb * rounds((double)(N / (kGemmTile * best.rg)) * tiles);
-  }
-  auto offer = [&](int wide, int rows, double fixed, double step1, double step) {
-    const double r = rounds(std::ceil(N / (double)rows) * ((tiles + wide - 1) / wide));
-    const double c = fixed + steps * r * (r > 1 ? step : step1);
-    if (c < cost) {
-      cost = c;
+  double least = 1e30;
+  auto offer = [&](int wide, const Times &t, double wgs, double k_steps, double stream) {
+    const double rounds = wgs / 256, whole = std::ceil(rounds);
+    const double loop = k_steps * (rounds <= 1 ? t.first : t.round * (whole + t.shared * (rounds - whole)));
+    const double us = t.fixed + std::max(loop, stream);
+    if (us < least) {
+      least = us;
       best.wide = wide;
     }
   };
+  // skinny: K split over 4 / rg waves; large weights at 7 TB/s at most (the
+  // other kernels read them faster: gate/up at hidden 2048, one tile, 1.1 us)
+  if (best.rg > 0)
+    offer(0, kSkinny[packed][use], (double)(N / (kGemmTile * best.rg)) * tiles, steps * best.rg / 4.0,
+          (double)N * K * 2 / 7e6);
   if ((uint64_t)N * K * 2 >= (1ull << 32) || (uint64_t)Tpad * K * 2 >= (1ull << 32)) return best;   // 32-bit offsets
+  auto wgs = [&](int rows, int wide) { return std::ceil(N / (double)rows) * ((tiles + wide - 1) / wide); };
   if (packed) {
-    if (K % 256 == 0) {
-      const double fixed = f16 ? 4.2 : 3.8;
-      offer(1, 128, fixed, 0.16, 0.19);
-      offer(2, 128, fixed, 0.235, 0.275);
-      offer(4, 128, fixed, 0.55, 0.55);
-    }
+    if (K % 256 == 0)
+      for (int i = 0; i < 3; ++i) offer(1 << i, kRows[use][i], wgs(128, 1 << i), steps, 0);
   } else if (K % 128 == 0 && K >= 256) {
-    offer(2, 64, f16 ? 4.2 : 4.6, f16 ? 0.21 : 0.1, f16 ? 0.22 : 0.15);
-    offer(4, 128, 7.5, 0.65, 0.65);
+    offer(2, kTile[use][0], wgs(64, 2), steps, 0);
+    offer(4, kTile[use][1], wgs(128, 4), steps, 0);
   }
   return best;
 }

@@ -377,7 +377,7 @@ hpd_status hpd_verify_draft_step(const hpd_model_desc *model, const hpd_pmtp_des
     g.w0 = (const __bf16 *)pmtp->w_draft_gate_up;
     g.K = 2 * L.H;
     g.N = 2 * L.Id;
-    const hpd::GemmShape sg = hpd::choose_gemm(g.N, g.K, L.nbpad, true, true);
+    const hpd::GemmShape sg = hpd::choose_gemm(g.N, g.K, L.nbpad, true, true, hpd::kEpiSwiGLU);
     g.rg = sg.rg;
     g.wide = sg.wide;
     g.n_slices = g.N / (hpd::kGemmTile * g.rg);
@@ -399,7 +399,7 @@ hpd_status hpd_verify_draft_step(const hpd_model_desc *model, const hpd_pmtp_des
     r.w0 = (const __bf16 *)pmtp->w_draft_down;
     r.K = L.Id;
     r.N = L.H;
-    const hpd::GemmShape sr = hpd::choose_gemm(r.N, r.K, L.nbpad, true, true);
+    const hpd::GemmShape sr = hpd::choose_gemm(r.N, r.K, L.nbpad, true, true, hpd::kEpiResidual);
     r.rg = sr.rg;
     r.wide = sr.wide;
     r.n_slices = r.N / (hpd::kGemmTile * r.rg);

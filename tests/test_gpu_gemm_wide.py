@@ -2,8 +2,9 @@
 against the fp64 oracle.
 
 Token counts off the 32-token tile and off the kernels' 2- and 4-tile groups,
-K of one ring up to many, a hidden size above the prefetched sums of squares,
-and a K that only the skinny kernel takes (intermediate 384)."""
+K of one ring up to many, hidden sizes above the prefetched sums of squares, and
+a K that only the skinny kernel takes (intermediate 384).  KERNELS names the
+shape that each projection takes and so keeps every kernel covered."""
 
 import pytest
 import torch
@@ -12,6 +13,7 @@ from oracle.decode import decode_step
 from workloads import get_config, make_decode_inputs
 
 from ._gpu import BF16_MAX_ABS, BF16_REL_L2, announce, errors
+from .test_gemm_choice import choose_gemm
 from .test_gpu_decode import _check_cache, run_decode
 
 pytestmark = pytest.mark.gpu
@@ -27,8 +29,31 @@ def _need_gpu():
 SHAPES = [(69, 512, 1024, 16, 2),     # 277 tokens: 9 tiles
           (165, 512, 1536, 16, 8),    # 661: 21 tiles
           (250, 256, 384, 8, 2),      # 1,001: 32 tiles, one ring of K, down skinny
-          (255, 1024, 3072, 16, 2),   # 1,021: the 4-tile groups
-          (72, 2048, 1024, 8, 1)]     # 289: 64 sums of squares per token
+          (255, 1024, 3072, 16, 2),   # 1,021: 32
+          (72, 2048, 1024, 8, 1)]     # 289: 10 tiles, 64 sums of squares per token
+# the same, and the kernel (GemmShape.wide) of QKV, O, gate/up and down with packed and with row-major weights;
+# 17, 25 and 43 tiles leave 1, 1 and 3 tiles in the last group of 4
+KERNELS = [((135, 256, 2048, 8, 2), (0, 0, 2, 0), (0, 0, 4, 0)),
+           ((83, 512, 4096, 8, 2), (1, 0, 4, 0), (2, 0, 4, 0)),
+           ((131, 2048, 2048, 16, 2), (1, 2, 4, 2), (2, 2, 2, 2)),    # 64 sums of squares: past 4 tiles' 32
+           ((197, 1024, 1024, 64, 2), (4, 1, 2, 1), (4, 2, 2, 2)),
+           ((340, 2560, 1024, 8, 2), (2, 2, 4, 4), (2, 4, 2, 4))]     # 80: past 2 tiles' 64 too
+
+
+def kernels(shape, packed):
+    content, hidden, inter, hq, hkv = shape
+    tiles = (4 * content + 1 + 31) // 32
+    sizes = (("qkv", (hq + 2 * hkv) * 64, hidden), ("o", hidden, hq * 64), ("gate_up", 2 * inter, hidden),
+             ("down", hidden, inter))
+    return tuple(choose_gemm(use, n, k, tiles, packed)[1] for use, n, k in sizes)
+
+
+@pytest.mark.parametrize("packed", [True, False], ids=["packed", "torch"])
+@pytest.mark.parametrize("case", KERNELS, ids=lambda c: "-".join(map(str, c[0])))
+def test_every_kernel(case, packed):
+    shape, want_packed, want_torch = case
+    assert kernels(shape, packed) == (want_packed if packed else want_torch)
+    test_many_tokens(shape, packed)
 
 
 @pytest.mark.parametrize("packed", [True, False], ids=["packed", "torch"])
