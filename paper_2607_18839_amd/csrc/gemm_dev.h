@@ -117,6 +117,9 @@ __device__ __forceinline__ void load_post(const GemmArgs &g, int t, int tile, in
   }
 }
 
+// SwiGLU of one gate / up pair, the same in every kernel.
+__device__ __forceinline__ float swiglu(float gate, float up) { return gate / (1.0f + __expf(-gate)) * up; }
+
 // Writes the finished 32 x 32 tile `tile` for token t (this lane: rows
 // 8 (r / 4) + 4 half + r % 4 of the tile, see below) through epilogue EPI.
 template <int EPI>
@@ -179,8 +182,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const f32x16 &acc, E
         f16x4 mv;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float gt = acc[4 * i + r] * f, up = acc[4 * i + 8 + r] * f;
-          mv[r] = (_Float16)(t < g.T ? gt / (1.0f + __expf(-gt)) * up : 0.f);
+          mv[r] = (_Float16)(t < g.T ? swiglu(acc[4 * i + r] * f, acc[4 * i + 8 + r] * f) : 0.f);
         }
         const int col = tile * 16 + 8 * i + 4 * half;
         const int64_t off = g.act_packed ? packed_offset(t, col, g.I) : (int64_t)t * g.I + col;

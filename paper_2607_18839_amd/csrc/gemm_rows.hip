@@ -236,10 +236,7 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(GemmArgs g) {
         const float f = tok_f[n * kGemmTile + row];
         f16x4 mv;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float gt_f = gt[r] * f;
-          mv[r] = (_Float16)(t < g.T ? gt_f * __builtin_amdgcn_rcpf(1.0f + __expf(-gt_f)) * (up[r] * f) : 0.f);
-        }
+        for (int r = 0; r < 4; ++r) mv[r] = (_Float16)(t < g.T ? swiglu(gt[r] * f, up[r] * f) : 0.f);
         *(f16x4 *)(mrow + 128 * k) = mv;   // 16 rows on: 16 pieces of 8 elements further
       }
     } else {

@@ -10,6 +10,7 @@ import pytest
 import torch
 
 from oracle.decode import decode_step
+from paper_2607_18839_amd.torch_api import DecodeStep
 from workloads import get_config, make_decode_inputs
 
 from ._gpu import BF16_MAX_ABS, BF16_REL_L2, announce, errors
@@ -72,3 +73,38 @@ def test_many_tokens(shape, packed):
     print(f"{shape} packed {packed}: max abs {mx:.3e} rel L2 {rl:.3e}")
     assert mx <= BF16_MAX_ABS and rl <= BF16_REL_L2, (mx, rl)
     _check_cache(inp, pk, pv, nk, nv)
+
+
+@pytest.mark.parametrize("shape", [(69, 512, 1024), (340, 512, 1536), (83, 512, 4096)],
+                         ids=lambda s: "-".join(map(str, s)))
+def test_swiglu_is_the_same_in_every_kernel(shape):
+    """Hidden values that are powers of two and one weight per gate, up and down
+    row: every product and sum is exact, so that the packed kernels of 1, 2 and
+    4 token tiles and the row-major ones can differ in SwiGLU itself alone."""
+    content, hidden, inter = shape
+    announce(f"swiglu {shape}")
+    T, g = 4 * content + 1, torch.Generator().manual_seed(content)
+    wide = kernels((content, hidden, inter, 8, 2), True)[2]
+    assert wide == {69: 1, 340: 2, 83: 4}[content]
+
+    def one_per_row(rows, cols, values):
+        w = torch.zeros(rows, cols)
+        w[torch.arange(rows), torch.randint(cols, (rows,), generator=g)] = values
+        return w.bfloat16().cuda()
+
+    weights = dict(w_qkv=torch.randn(12 * 64, hidden, generator=g).bfloat16().cuda(),
+                   w_o=torch.zeros(hidden, 512).bfloat16().cuda(),
+                   w_gate=one_per_row(inter, hidden, 2 * torch.randn(inter, generator=g)),
+                   w_up=one_per_row(inter, hidden, torch.randn(inter, generator=g)),
+                   w_down=one_per_row(hidden, inter, torch.ones(hidden)))
+    h = torch.randint(-2, 2, (T, hidden), generator=g).float().exp2()
+    h *= torch.randint(2, (T, hidden), generator=g) * 2 - 1
+    out = []
+    for packed in (True, False):
+        step = DecodeStep(8, 2, [64], [0] * (content + 1), [1] + [4] * content, [0] * (content + 1),
+                          {n: [w] for n, w in weights.items()}, hidden, inter, packed=packed)
+        kv = [[torch.zeros(n, 2, 64, dtype=torch.bfloat16, device="cuda")] for n in (64, 64, T, T)]
+        out.append(step(h.cuda(), *kv))
+    m = out[0] - h.cuda()
+    assert torch.isfinite(m).all() and (m != 0).float().mean() > 0.9
+    assert torch.equal(out[0], out[1]), int((out[0] != out[1]).sum())
