@@ -425,7 +425,8 @@ const char *hpd_kernel_kind_name(int kind);
 /* Phase isolation (benchmark support, process-wide, default off).  When on,
  * the bf16 attention enqueues its private work items as a launch of their
  * own (kind 1) after the shared-prefix launch (kind 0) instead of running
- * both in one launch, so each phase can be timed and profiled on its own.
+ * both in one launch, so each phase can be timed and profiled on its own (the
+ * same kernel, with the same work lists where the plan has them).
  * Results are bit-identical either way.  Not to be changed while a step is
  * being enqueued or captured. */
 hpd_status hpd_attn_phase_isolation(int enable);

@@ -1083,13 +1083,17 @@ __global__ __launch_bounds__(512) void balanced_ring_kernel(AttnArgs a, const in
   // (opaque, so that no item's per-lane values are kept over the loops)
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
-  for (int item = wd.x; item < wd.y; ++item) {
+  // (no items of one kind: the other phase on its own)
+  const int shared1 = a.n_shared > 0 ? wd.y : wd.x, priv1 = a.n_private > 0 ? wd.w : wd.z;
+  for (int item = wd.x; item < shared1; ++item) {
     ring_item<FORK>(a, shared_item(a, item), tid, lds);
     ring_barrier();   // every wave is done with the epilogue's scratch
   }
   asm volatile("" : "+v"(tid));
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int pi = wd.z + wave; pi < wd.w; pi += kPrivMaxPerWG)
+  // (an item's last LDS reads, write_f16's, have returned when it is done: its
+  // stores wait for them; so the next one's copies may fill the wave's tiles)
+  for (int pi = wd.z + wave; pi < priv1; pi += kPrivMaxPerWG)
     private_item_ring(a, pi, tid & 63, lds + wave * kPrivWaveBytes);
 }
 
@@ -1308,8 +1312,8 @@ hipError_t launch_branch_attention(const Plan &P, const void *q, const void *sha
     // Private items per workgroup: the fewest that still fit the grid on
     // the chip in one round (one workgroup per CU: the launch's LDS), so
     // that the items spread over the CUs the shared items leave free.  A grid
-    // of more than one round (plans of private items only, and the phases on
-    // their own: the others have lists, balanced_ring_kernel) takes 4 each.
+    // of more than one round (plans of private items only: the others have
+    // lists, balanced_ring_kernel) takes 4 each.
     auto fit = [&](AttnArgs &x) {
       for (x.priv_per_wg = 1; x.priv_per_wg < kPrivMaxPerWG; ++x.priv_per_wg)
         if (grid(x) <= num_cus()) break;
@@ -1317,23 +1321,26 @@ hipError_t launch_branch_attention(const Plan &P, const void *q, const void *sha
       if (!x.priv_first) x.priv_per_wg = 4;
       x.priv_slots = priv_slots(x);
     };
-    fit(a);
-    auto ring = P.has_fork ? shared_prefix_ring_kernel<true> : shared_prefix_ring_kernel<false>;
+    auto run = [&](int kind, AttnArgs x) {
+      if (P.num_wg > 0) {
+        x.reg.on = 0;   // the lists' items are in an order of their own
+        launch(kind, P.has_fork ? balanced_ring_kernel<true> : balanced_ring_kernel<false>,
+               dim3((P.num_wg + 7) / 8 * 8), dim3(512), stream, x,
+               (const int4 *)((const unsigned char *)workspace + P.off_wg), P.num_wg);
+      } else {
+        fit(x);
+        launch(kind, P.has_fork ? shared_prefix_ring_kernel<true> : shared_prefix_ring_kernel<false>, dim3(grid(x)),
+               dim3(512), stream, x);
+      }
+    };
     if (attn_phase_isolation()) {
       AttnArgs sh = a, pr = a;
       sh.n_private = 0;
       pr.n_shared = 0;
-      fit(sh);
-      fit(pr);
-      if (sh.n_shared > 0) launch(KK_SHARED, ring, dim3(grid(sh)), dim3(512), stream, sh);
-      if (pr.n_private > 0) launch(KK_PRIVATE, ring, dim3(grid(pr)), dim3(512), stream, pr);
-    } else if (P.num_wg > 0) {
-      a.reg.on = 0;
-      launch(KK_SHARED, P.has_fork ? balanced_ring_kernel<true> : balanced_ring_kernel<false>,
-             dim3((P.num_wg + 7) / 8 * 8), dim3(512), stream, a,
-             (const int4 *)((const unsigned char *)workspace + P.off_wg), P.num_wg);
-    } else if (grid(a) > 0) {
-      launch(KK_SHARED, ring, dim3(grid(a)), dim3(512), stream, a);
+      if (sh.n_shared > 0) run(KK_SHARED, sh);
+      if (pr.n_private > 0) run(KK_PRIVATE, pr);
+    } else if (a.n_shared + a.n_private > 0) {
+      run(KK_SHARED, a);
     }
   } else {
     // one launch, as for bf16; phase isolation: the shared items, then the

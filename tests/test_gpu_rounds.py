@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from oracle.attention import attention_for_batch
+from paper_2607_18839_amd import _lib
 from workloads.gen import attn_batch_from_structure
 
 from ._gpu import announce, assert_parity, run_batch
@@ -35,11 +36,8 @@ CASES = [(70, 150, 6, 40, 16, 8),      # more items than workgroups, none longer
          (1, 900, 120, 200, 64, 8)]    # one page
 
 
-@pytest.mark.parametrize("fork", [False, True], ids=["whole", "fork"])
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
-def test_more_than_one_round(case, fork):
-    pages, prefix_hi, branches, past_hi, hq, hkv = case
-    announce(f"rounds {case} fork {fork}")
+def structure(case, fork):
+    pages, prefix_hi, branches, past_hi, _, _ = case
     rng = np.random.default_rng(17)
     prefix = rng.integers(1, prefix_hi + 1, pages)
     prefix[0] = prefix_hi
@@ -51,8 +49,32 @@ def test_more_than_one_round(case, fork):
               past_len=rng.integers(0, past_hi + 1, len(page)).astype(np.int32))
     if fork:
         st["fork_len"] = np.array([rng.integers(0, prefix[p] + 1) for p in page], np.int32)
-    b = attn_batch_from_structure(st, hq, hkv, 64, "bf16", 5)
+    return st
+
+
+@pytest.mark.parametrize("fork", [False, True], ids=["whole", "fork"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_more_than_one_round(case, fork):
+    announce(f"rounds {case} fork {fork}")
+    st = structure(case, fork)
+    b = attn_batch_from_structure(st, *case[4:], 64, "bf16", 5)
     O, lse = run_batch(b, fork_len=st.get("fork_len"))
     Oref, lref = attention_for_batch(b)
     assert_parity(O, Oref, "bf16", f"rounds {case}")
     assert np.abs(lse - lref).max() <= LSE_BOUND
+
+
+@pytest.mark.parametrize("fork", [False, True], ids=["whole", "fork"])
+def test_phases_on_their_own(fork):
+    """Phase isolation runs the same lists, each launch one kind of item: the same bits."""
+    announce(f"rounds, phases on their own, fork {fork}")
+    st = structure(CASES[1], fork)
+    b = attn_batch_from_structure(st, *CASES[1][4:], 64, "bf16", 5)
+    got = []
+    try:
+        for isolated in (False, True):
+            _lib.hpd_attn_phase_isolation(isolated)
+            got.append(run_batch(b, fork_len=st.get("fork_len")))
+    finally:
+        _lib.hpd_attn_phase_isolation(False)
+    assert all(np.array_equal(x, y) for x, y in zip(*got))
