@@ -2,6 +2,8 @@
 workgroups (the planner deals them out, balanced_ring_kernel runs them),
 against the fp64 oracle."""
 
+from dataclasses import replace
+
 import numpy as np
 import pytest
 import torch
@@ -10,7 +12,9 @@ from oracle.attention import attention_for_batch
 from paper_2607_18839_amd import _lib
 from workloads.gen import attn_batch_from_structure
 
-from ._gpu import announce, assert_parity, run_batch
+from ._gpu import LSE_ABS, announce, assert_parity, run_batch, to_dev
+from .test_gpu_paged import _pool_rows, _scatter
+from .test_kv_pool import _pool_layout
 
 pytestmark = pytest.mark.gpu
 
@@ -21,11 +25,15 @@ def _need_gpu():
         pytest.skip("no GPU")
 
 
-# A shared item's row sums add probabilities rounded to bf16 (relative error at
-# most 2^-9 each, all positive), so a log-sum-exp moves by at most ln(1 + 2^-9),
-# which short prefixes come near (a long sum averages the roundings out); fp32
-# products and sums add less than 1e-5.
-LSE_BOUND = 2.0 ** -9 + 1e-5
+# A shared item's row sums add probabilities rounded to bf16 (8 significant bits:
+# relative error at most 2^-8 each, all positive), so a log-sum-exp moves by at
+# most ln(1 + 2^-8); fp32 products and sums add less than 1e-5.  Rows that see only
+# a few prefix keys come near it (measured 1.3e-3 at 7 keys); over 64 and more keys
+# the roundings average out and the suite's own bar holds (9.5e-4).
+def lse_bound(st):
+    shared = st["fork_len"] if "fork_len" in st else st["prefix_len"][st["branch_page"]]
+    return np.where(np.repeat(shared, st["num_new"]) >= 64, LSE_ABS, 2.0 ** -8 + 1e-5)[:, None]
+
 
 # pages, longest prefix, branches per page, longest private history, query heads, kv heads
 CASES = [(70, 150, 6, 40, 16, 8),      # more items than workgroups, none longer than two pairs of tiles
@@ -34,6 +42,8 @@ CASES = [(70, 150, 6, 40, 16, 8),      # more items than workgroups, none longer
          (36, 500, 20, 130, 12, 2),    # G = 6: tokens cross row groups
          (6, 700, 60, 900, 4, 4),      # G = 1, mostly private items
          (1, 900, 120, 200, 64, 8)]    # one page
+PAGED = CASES[1:3] + [(8, 9000, 20, 100, 16, 2),    # pieces of 64 tiles at most: a wave's table entries
+                      (5, 2000, 24, 40, 16, 8)]     # short histories, dealt out by half rounds
 
 
 def structure(case, fork):
@@ -61,7 +71,58 @@ def test_more_than_one_round(case, fork):
     O, lse = run_batch(b, fork_len=st.get("fork_len"))
     Oref, lref = attention_for_batch(b)
     assert_parity(O, Oref, "bf16", f"rounds {case}")
-    assert np.abs(lse - lref).max() <= LSE_BOUND
+    assert (np.abs(lse - lref) <= lse_bound(st)).all(), np.abs(lse - lref).max()
+
+
+@pytest.mark.parametrize("fork", [False, True], ids=["whole", "fork"])
+@pytest.mark.parametrize("case", PAGED, ids=lambda c: "-".join(map(str, c)))
+def test_more_than_one_round_paged(case, fork):
+    announce(f"rounds paged {case} fork {fork}")
+    st = structure(case, fork)
+    b = attn_batch_from_structure(st, *case[4:], 64, "bf16", 6)
+    _, pg = _pool_layout(st, 64, np.random.default_rng(4))
+    rows = dict(zip("sp", _pool_rows(st, pg)))
+    pools = {n: to_dev(_scatter(getattr(b, n), rows[n[0]], pg["num_blocks"] * 64, np.uint16(0x7FC0)), "bf16")
+             for n in ("shared_k", "shared_v", "priv_k", "priv_v")}
+    O, lse = run_batch(b, fork_len=st.get("fork_len"), paged=pg, **pools)
+    Oref, lref = attention_for_batch(b)
+    assert_parity(O, Oref, "bf16", f"rounds paged {case}")
+    assert (np.abs(lse - lref) <= lse_bound(st)).all(), np.abs(lse - lref).max()
+
+
+def test_at_the_scratch_limit():
+    """24 pages whose pieces would pass the library's own scratch: the even splits
+    are dealt out, hpd_branch_attn_step_noalloc takes the plan, and its results
+    are those of the workspace entry point."""
+    announce("rounds at the scratch limit")
+    rng = np.random.default_rng(4)
+    prefix, n = rng.integers(1024, 4097, 24), rng.integers(17, 34, 24)
+    page = np.repeat(np.arange(24), n)
+    past = np.minimum(700, np.exp(rng.normal(np.log(128), 1, len(page)))).astype(np.int32)
+    st = dict(prefix_len=prefix.astype(np.int32), branch_page=page.astype(np.int32),
+              num_new=np.full(len(page), 4, np.int32), past_len=past)
+    b = attn_batch_from_structure(st, 16, 2, 64, "bf16", 7)
+    plan = _lib.hpd_plan_create(16, 2, *(st[k] for k in ("prefix_len", "branch_page", "num_new", "past_len")))
+    limit = _lib.HPD_NOALLOC_SCRATCH_BYTES
+    assert limit - (1 << 20) < plan.workspace_bytes <= limit
+    want, want_lse = run_batch(b)
+    t = [to_dev(getattr(b, f), "bf16") for f in ("q", "shared_k", "shared_v", "priv_k", "priv_v")]
+    out, lse = torch.empty_like(t[0]), torch.empty(t[0].shape[:2], device="cuda")
+    _lib.hpd_branch_attn_step_noalloc(plan, *(x.data_ptr() for x in t), out.data_ptr(), lse.data_ptr(),
+                                      torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.double().cpu().numpy(), want) and np.array_equal(lse.double().cpu().numpy(), want_lse)
+    for p in (0, 11, 23):   # against the oracle: pages of their own
+        o = np.flatnonzero(page == p)
+        keep = dict(prefix_len=st["prefix_len"][p:p + 1], branch_page=np.zeros(len(o), np.int32),
+                    num_new=st["num_new"][o], past_len=past[o])
+        rows = np.cumsum(np.concatenate([[0], past + 4]))
+        sh = np.cumsum(np.concatenate([[0], prefix]))
+        one = replace(b, **keep, q=b.q[4 * o[0]:4 * o[-1] + 4],
+                      **{k: getattr(b, k)[sh[p]:sh[p + 1]] for k in ("shared_k", "shared_v")},
+                      **{k: getattr(b, k)[rows[o[0]]:rows[o[-1] + 1]] for k in ("priv_k", "priv_v")})
+        ref, _ = attention_for_batch(one)
+        assert_parity(want[4 * o[0]:4 * o[-1] + 4], ref, "bf16", f"page {p}")
 
 
 @pytest.mark.parametrize("fork", [False, True], ids=["whole", "fork"])
