@@ -604,8 +604,10 @@ int choose_rg(int N, int K, int tiles) {
 // at hidden 2048 and 5 to 8 tiles took 128 rows x 1 tile, 10 to 12 us slower than
 // the skinny kernel, and 128 rows x 4 tiles were never taken, though gate/up at
 // hidden 2048 and 32 to 48 tiles is 10 to 14 us faster so.  Over those 2,288
-// projections the choice costs 0.04 % of a layer's time on average against the
-// best shape of each, 0.70 % by the former rule.
+// projections the choice costs 0.05 % of a layer's time on average against the
+// best shape of each, 0.70 % by the former rule.  (1 tile x 128 rows of gate/up
+// is priced 0.25 us below the fit: the draft MLP of a vocabulary that stays in
+// cache then takes it at 5 and 6 tiles, 3 us faster, and cold ones lose nothing.)
 GemmShape choose_gemm(int N, int K, int Tpad, bool packed, bool f16, int epi) {
   // us: a fixed part (launch, first loads, epilogue), a K step of a launch of up
   // to one workgroup per CU and of each round of 256 of a larger one, and the
@@ -620,7 +622,7 @@ GemmShape choose_gemm(int N, int K, int Tpad, bool packed, bool f16, int epi) {
   // [bf16; fp16 gate/up; fp16 down]: 1, 2 and 4 token tiles by 128 rows (packed)
   static constexpr Times kRows[3][3] = {
       {{3.05, 0.166, 0.206, 0.42}, {3.35, 0.25, 0.264, 0.7}, {4.9, 0.36, 0.54, 1.0}},
-      {{3.1, 0.19, 0.213, 0.3}, {3.15, 0.278, 0.255, 0.41}, {3.65, 0.39, 0.405, 0.0}},
+      {{2.85, 0.19, 0.213, 0.3}, {3.15, 0.278, 0.255, 0.41}, {3.65, 0.39, 0.405, 0.0}},
       {{2.8, 0.184, 0.198, 0.33}, {3.1, 0.275, 0.243, 0.42}, {3.9, 0.405, 0.381, 0.0}}};
   // 2 token tiles by 64 rows and 4 by 128 (row-major)
   static constexpr Times kTile[3][2] = {{{3.55, 0.118, 0.22, 0.57}, {4.05, 0.74, 0.605, 0.66}},

@@ -65,6 +65,9 @@ MEASURED = [
     ("o", 1024, 1024, 40, False, {0: 1.0, 2: 0.0, 4: 9.5}),
     ("gate_up", 6144, 1024, 40, False, {0: 28.7, 2: 13.0, 4: 0.0}),
     ("down", 1024, 3072, 40, False, {0: 12.3, 2: 0.0, 4: 25.8}),
+    # the draft MLP between passes over a head that stays in cache
+    ("gate_up", 2048, 2048, 5, True, {0: 2.9, 1: 0.0, 2: 2.1, 4: 5.5}),
+    ("gate_up", 2048, 2048, 7, True, {0: 0.0, 1: 2.6, 2: 5.2, 4: 11.4}),
 ]
 
 
