@@ -25,19 +25,12 @@ HIP_SOURCES = ["attn_kernels.hip", "gemm_kernels.hip", "gemm_tile.hip", "gemm_ro
 CXX_SOURCES = ["plan.cpp", "kv_pool.cpp", "scheduler.cpp"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
-# Packed fp32 VALU forms are disabled for all device code.
+# Packed fp32 VALU forms are disabled for all device code.  MFMA results
+# are kept in architectural VGPRs (the accumulator-register form made the
+# allocator shuttle accumulators through v_accvgpr moves inside the k loops).
 HIP_FLAGS = COMMON + [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang",
-                      "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
-# MFMA results are kept in architectural VGPRs (the accumulator-register form
-# made the allocator shuttle accumulators through v_accvgpr moves inside the k
-# loops), except in kernels whose accumulators and operand rings together pass
-# 256 registers.
-VGPR_MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
-AGPR_SOURCES = {"gemm_rows.hip"}
-
-
-def hip_flags(source):
-    return HIP_FLAGS + ([] if os.path.basename(source) in AGPR_SOURCES else VGPR_MFMA)
+                      "-packed-fp32-ops", "-mllvm", "-amdgpu-mfma-vgpr-form",
+                      "-Wno-unused-command-line-argument"]
 
 
 def _run(cmd):
@@ -54,7 +47,7 @@ def build(verbose=False):
     for s in HIP_SOURCES:
         src = os.path.join(CSRC, s)
         if os.path.exists(src):
-            jobs.append([HIPCC] + hip_flags(src) + ["-c", src, "-o", os.path.join(BUILD, s + ".o")])
+            jobs.append([HIPCC] + HIP_FLAGS + ["-c", src, "-o", os.path.join(BUILD, s + ".o")])
     for s in CXX_SOURCES:
         jobs.append(["g++"] + COMMON + ["-Wall", "-c", os.path.join(CSRC, s), "-o", os.path.join(BUILD, s + ".o")])
     with cf.ThreadPoolExecutor(max_workers=min(8, len(jobs))) as ex:
@@ -65,7 +58,7 @@ def build(verbose=False):
     tmp = LIB + ".tmp"
     _run([HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp] + objs)
     os.replace(tmp, LIB)
-    _run([HIPCC] + HIP_FLAGS + VGPR_MFMA + ["-o", PEAKS + ".tmp", os.path.join(CSRC, "peaks.hip")])
+    _run([HIPCC] + HIP_FLAGS + ["-o", PEAKS + ".tmp", os.path.join(CSRC, "peaks.hip")])
     os.replace(PEAKS + ".tmp", PEAKS)
     return LIB
 
