@@ -227,13 +227,13 @@ __device__ __forceinline__ void ds_read_tr16_half(u32x2t (&vr)[8], const unsigne
     ds_read_tr16_half<H, I + 1>(vr, vb0, vb1);
   }
 }
-// All but the newest N of the wave's LDS reads have returned (they return in
-// order), among them v.
-template <int N>
-__device__ __forceinline__ void lds_wait_tr(u32x2t (&v)[8]) {
-  asm volatile("s_waitcnt lgkmcnt(%8)"
-               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
-               : "n"(N)
+// The wave's LDS reads have returned, among them v (one tile's, by halves).
+__device__ __forceinline__ void lds_wait_tr(u32x2t (&v)[2][8]) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(v[0][0]), "+v"(v[0][1]), "+v"(v[0][2]), "+v"(v[0][3]), "+v"(v[0][4]), "+v"(v[0][5]),
+                 "+v"(v[0][6]), "+v"(v[0][7]), "+v"(v[1][0]), "+v"(v[1][1]), "+v"(v[1][2]), "+v"(v[1][3]),
+                 "+v"(v[1][4]), "+v"(v[1][5]), "+v"(v[1][6]), "+v"(v[1][7])
+               :
                : "memory");
 }
 
@@ -494,8 +494,7 @@ template <typename T> struct WaveAttn {
     Frag<T> pf[4];
 #pragma unroll
     for (int st = 0; st < 4; ++st) from_f32(pf[st], p + 8 * st);
-    lds_wait_tr<0>(vr[0]);
-    lds_wait_tr<0>(vr[1]);
+    lds_wait_tr(vr);
     // matrix core: this tile's PV and row sums
 #pragma unroll
     for (int b = 0; b < 2; ++b)
@@ -1019,7 +1018,7 @@ __device__ __forceinline__ void private_item_ring(const AttnArgs &a, int item, i
 #pragma unroll
     for (int r = 0; r < 16; ++r) { s_cur[0][r] = s_next[0][r]; s_cur[1][r] = s_next[1][r]; }
     w.step_frags<true>(false, ka[1], lds + kTileBytes, voff, s_cur, s_next, key0 + 64, limit, key0 + 128 > wmin,
-                              a.c);
+                       a.c);
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the V tiles are consumed; tile 0 becomes write scratch
   // partial row of the wave's row `lane` (the planner keeps partial rows below 2^31)
@@ -1068,9 +1067,9 @@ __global__ __launch_bounds__(512) void shared_prefix_ring_kernel(AttnArgs a) {
 // items 8 at a time, one per wave.  Handed out in launch order instead (each
 // XCD a contiguous run of equal splits, the private workgroups behind them)
 // the CUs finish far apart: 16 pages have items of 9 to 18 pairs of tiles, 24
-// pages with fork points up to 27.  The bound is the loop's time per pair
-// (about 1.4 us with all CUs busy, MFMAs and softmax hardly overlapping;
-// placing 2 or 3 MFMAs behind every 4 exponentials measured no faster).  The
+// pages with fork points up to 27.  The bound is the loop's time per pair (1.4
+// to 1.5 us with all CUs busy, MFMAs and softmax hardly overlapping; placing 2
+// or 3 MFMAs behind every 4 exponentials measured no faster).  The
 // private items first, or on every other workgroup first: no faster.
 // Attention layers, with their merge: 16 pages of 4 to 32 branches 40.4 -> 34.3
 // us, 24 such pages with fork points and paged K/V 57.9 -> 47.6 us.
