@@ -286,13 +286,25 @@ def _to_pool(torch, t, rows, n_rows):
 
 
 def code_digest(path):
-    """sha256 of a C++/HIP source with its comments, trailing blanks and empty
-    lines removed: an edit of the comments alone leaves it unchanged."""
+    """sha256 of a C++/HIP source and of the headers beside it that it includes,
+    with comments, trailing blanks and empty lines removed: an edit of the
+    comments alone leaves it unchanged."""
     import hashlib
     import re
-    text = re.sub(r"/\*.*?\*/", "", open(path, encoding="utf-8").read(), flags=re.S)
-    lines = [re.sub(r"//.*$", "", l).rstrip() for l in text.splitlines()]
-    return hashlib.sha256("\n".join(l for l in lines if l).encode()).hexdigest()
+    seen = []
+
+    def code(p):
+        text = re.sub(r"/\*.*?\*/", "", open(p, encoding="utf-8").read(), flags=re.S)
+        lines = [re.sub(r"//.*$", "", l).rstrip() for l in text.splitlines()]
+        out = ["\n".join(l for l in lines if l)]
+        for name in re.findall(r'^#include "([^"]+)"', out[0], re.M):
+            h = os.path.join(os.path.dirname(p), name)
+            if h not in seen and os.path.exists(h):
+                seen.append(h)
+                out += code(h)
+        return out
+
+    return hashlib.sha256("\n".join(code(path)).encode()).hexdigest()
 
 
 def _traffic(kind, workload="c4"):

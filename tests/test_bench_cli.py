@@ -60,6 +60,19 @@ def test_code_digest_ignores_comments_only(tmp_path):
     assert bench.code_digest(str(a)) == bench.code_digest(str(b)) != bench.code_digest(str(c))
 
 
+def test_code_digest_covers_the_headers(tmp_path):
+    sys.path.insert(0, ROOT)
+    import bench
+    a, h = tmp_path / "a.hip", tmp_path / "h.h"
+    a.write_text('#include <string>\n#include "h.h"\n#include "elsewhere.h"\nint g() { return f(); }\n')
+    h.write_text('#include "h.h"\nint f();\n')
+    before = bench.code_digest(str(a))
+    h.write_text('#include "h.h"\nint f();   // a note\n')
+    assert bench.code_digest(str(a)) == before
+    h.write_text('#include "h.h"\nlong f();\n')
+    assert bench.code_digest(str(a)) != before
+
+
 def test_box_peak_only_for_the_measured_units():
     """The box's own peaks cover bf16 MFMA and HBM reads: a bf16 or HBM
     roofline gets the second denominator, an fp32 one gets none."""
